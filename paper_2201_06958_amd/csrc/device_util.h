@@ -277,14 +277,6 @@ __device__ __forceinline__ double wave_max_d(double v) {
 }
 
 // ------------------------------------------------ Cholesky factor and inverse by one wave
-// Value of v held by lane `src` (uniform), as a wave-uniform double.
-__device__ __forceinline__ double lane_bcast(double v, int src) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, src);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
 // 1/sqrt(x) for x > 0 to full FP64 accuracy: the hardware estimate and two Newton steps.
 __device__ __forceinline__ double rsqrt_nr(double x) {
   double r = __builtin_amdgcn_rsq(x);
@@ -348,9 +340,9 @@ __device__ __forceinline__ bool wave_chol_block(double* A, double* Li, int ld, i
   }
 #pragma unroll
   for (int k = 0; k < S; ++k) {
-    const double w = v[k] * rcp_nr(lane_bcast(v[k], k));
+    const double w = v[k] * rcp_nr(lane_get(v[k], k));
 #pragma unroll
-    for (int i = k + 1; i < S; ++i) v[i] = fma(-lane_bcast(v[i], k), w, v[i]);
+    for (int i = k + 1; i < S; ++i) v[i] = fma(-lane_get(v[i], k), w, v[i]);
   }
   // the pivots, one a lane: tested and their roots taken at once (a branch or a root per
   // step would lengthen every step)
@@ -361,7 +353,7 @@ __device__ __forceinline__ bool wave_chol_block(double* A, double* Li, int ld, i
   const double rl = rsqrt_nr(fmax(d, 1e-300));
   double rs[S];
 #pragma unroll
-  for (int i = 0; i < S; ++i) rs[i] = lane_bcast(rl, i);
+  for (int i = 0; i < S; ++i) rs[i] = lane_get(rl, i);
   // lane c < 16: entries i <= c of column c are D L^T (row c of L); lane 16 + c: column c of
   // the inverse of the unit lower factor. One store per i for both, predicated per lane
   // (`lim` in a vector register: a scalar test would branch around every store)
@@ -385,17 +377,16 @@ __device__ __forceinline__ bool wave_chol16(double* A, double* Li, int ld, int k
   return wave_chol_block<16>(A, Li, ld, k0, n, dmax);
 }
 
-// Lower Cholesky factor of the SPD n x n matrix A (n <= 64, LDS, row stride ld) in place,
+// Lower Cholesky factor of the SPD n x n matrix A (n <= 32, LDS, row stride ld) in place,
 // zeros above, its inverse Li and, with Gi, the inverse Gi = Li^T Li of A, all of row
-// stride ld, by one full wave (no lane may be masked off). 16 x 16 blocks: the diagonal
-// blocks in registers, everything else as matrix products. Returns false if a pivot is not
-// positive or is below TDB_PIVOT_FLOOR times the largest diagonal entry; Li and Gi are
-// then not all formed.
+// stride ld, by one full wave (no lane may be masked off), for second-order streams. 16 x 16
+// blocks: the diagonal blocks in registers, everything else as matrix products. Returns false
+// if a pivot is not positive or is below TDB_PIVOT_FLOOR times the largest diagonal entry; Li
+// and Gi are then not all formed.
 // Bound by the dependent steps of the elimination. In registers of one lane per row, with
-// a second substitution for the inverse and LDS loops above rank 32, it took 6.0 us at
-// n = 16, 16.7 at 32 and 92 at 33; this form takes 3.5, 9.2 and 17.2, and with the short last
-// block's elimination cut to 4 or 8 steps 1.3 at n = 3 (3.1 with 16), 1.8 at 8, 5.6 at 17
-// (8.4) and at 20.
+// a second substitution for the inverse, it took 6.0 us at n = 16 and 16.7 at 32; this form
+// takes 3.5 and 9.2, and with the short last block's elimination cut to 4 or 8 steps 1.3 at
+// n = 3 (3.1 with 16), 1.8 at 8, 5.6 at 17 (8.4) and at 20.
 template <int NB>
 __device__ __forceinline__ bool wave_chol_inv_nb(double* A, int n, int ld, double* Li, double* Gi) {
   const int l = threadIdx.x & 63;
@@ -485,14 +476,239 @@ __device__ __forceinline__ bool wave_chol_inv_nb(double* A, int n, int ld, doubl
   return true;
 }
 
-// (the larger forms out of line: they are rare and long; they also take matrices in
-// global memory)
-static __device__ __attribute__((noinline)) bool wave_chol_inv_big(double* A, int n, double* Li, double* Gi) {
-  return n <= 48 ? wave_chol_inv_nb<3>(A, n, n, Li, Gi) : wave_chol_inv_nb<4>(A, n, n, Li, Gi);
+// ------------------------------------------------ the same, operation by operation
+// The forms for the state of a third-order stream: a stream that holds directions near the
+// noise floor turns one rounding of these matrices into changes of its reconstruction that can
+// be seen, so each entry goes through one fixed sequence of operations, whatever the split
+// over lanes and matrix instructions: right-looking, one column after another,
+//   l_jj = a_jj r, l_ij = a_ij r with r = rsqrt(a_jj), a_ik <- fma(-l_ij, l_kj, a_ik),
+// and for each column of the inverse, x_j <- x_j r, x_i <- fma(-l_ij, x_j, x_i); above 32 rows
+//   l_jj = sqrt(a_jj), l_ij = a_ij / l_jj, x_jj = 1 / l_jj, x_ij = -(sum_k l_ik x_kj) / l_ii.
+// A 16x16x4 FP64 product is an ascending chain of fused multiply-adds, so it takes the place
+// of any run of such updates.
+// Bound by the dependent steps. With Gi: 1.0 us at n = 4, 1.6 at 8, 3.4 at 16, 5.9 at 18, 9.9 at
+// 32, 36 at 33 and 62 at 64; one lane per row with the inverse as a second substitution took
+// 5.7, 5.8, 6.0, 16.3 and 16.8, and with loops over LDS above 32 rows 95 and 388.
+
+// Largest of the lanes' values (none of them NaN), in every lane.
+__device__ __forceinline__ double wave_max_dpp(double v) {
+  v = fmax(v, dpp_get<0xB1>(v));
+  v = fmax(v, dpp_get<0x4E>(v));
+  v = fmax(v, dpp_get<0x141>(v));
+  v = fmax(v, dpp_get<0x140>(v));
+  return fmax(fmax(lane_get(v, 0), lane_get(v, 16)), fmax(lane_get(v, 32), lane_get(v, 48)));
 }
+
+// Columns k0 .. k0 + S - 1 of the factor of A, n <= 32 (row-major, stride n): lane c < 32
+// holds row c, lane 32 + c column c of the inverse, so that a step's broadcasts serve both.
+// Li holds, in the rows of the panel, what the earlier panels have subtracted. RD: the
+// inverse's rows are scaled by 1 / l_jj instead of r. Rows and columns from n on are the
+// identity's. Returns false if a pivot is not positive or not above `floor`.
+template <int S, bool RD>
+__device__ __forceinline__ bool wave_panel(double* A, double* Li, int n, int k0, double floor) {
+  const int l = threadIdx.x & 63, c = l & 31;
+  const bool isX = l >= 32;
+  double v[S], piv[S];
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    const int q = k0 + j, qc = min(q, n - 1), cc = min(c, n - 1);
+    const double x = *(isX ? Li + qc * n + cc : A + cc * n + qc);
+    v[j] = (q < n && c < n && (isX ? c < k0 : c >= k0)) ? x : (c == q ? 1.0 : 0.0);
+  }
+#pragma unroll
+  for (int k = 0; k < S; ++k) {
+    piv[k] = lane_get(v[k], k0 + k);
+    const double pv = fmax(piv[k], 1e-300), r = rsqrt_nr(pv), lk = pv * r;
+    const double f = RD && isX ? 1.0 / lk : r;
+    v[k] = (!isX && c == k0 + k) ? lk : v[k] * f;
+#pragma unroll
+    for (int j = k + 1; j < S; ++j) v[j] = fma(-v[k], lane_get(v[k], k0 + j), v[j]);
+  }
+  bool ok = true;
+#pragma unroll
+  for (int k = 0; k < S; ++k) ok = ok && (k0 + k >= n || (piv[k] > floor && piv[k] > 0.0));
+  // one store per column for both, predicated per lane (`lim` in a vector register: a scalar
+  // test would branch around every store)
+  int lim = min(n - k0, S);
+  asm volatile("" : "+v"(lim));
+  double* dst = isX ? Li + k0 * n + c : A + c * n + k0;
+  const int step = isX ? n : 1;
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    const double x = (isX || k0 + j <= c) ? v[j] : 0.0;
+    if (c < n && j < lim) dst[j * step] = x;
+  }
+  wave_fence();
+  return ok;
+}
+
+// Gi = Li^T Li (n <= 16 NB, row stride n), sums over the rows in order.
+template <int NB>
+__device__ __forceinline__ void wave_inv_gram(const double* Li, double* Gi, int n) {
+  auto at = [&](int i, int j) {
+    const double x = Li[min(i, n - 1) * n + min(j, n - 1)];
+    return (i < n && j < n) ? x : 0.0;
+  };
+#pragma unroll
+  for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+    for (int jb = 0; jb <= ib; ++jb) {
+      const int i0 = 16 * ib, j0 = 16 * jb;
+      wd4 r = {0, 0, 0, 0};
+#pragma unroll
+      for (int kb = ib; kb < NB; ++kb)
+        r = mm16<16>([&](int i, int k) { return at(16 * kb + k, i0 + i); },
+                     [&](int k, int j) { return at(16 * kb + k, j0 + j); }, r);
+      each16(r, [&](int i, int j, double v) {
+        if (i0 + i < n && j0 + j < n) {
+          Gi[(i0 + i) * n + j0 + j] = v;
+          if (ib != jb) Gi[(j0 + j) * n + i0 + i] = v;
+        }
+      });
+    }
+}
+
+template <int S, bool RD>
+__device__ __forceinline__ bool wave_chol_inv_s(double* A, int n, double* Li, double* Gi) {
+  const int l = threadIdx.x & 63;
+  const double x = A[min(l, n - 1) * (n + 1)];
+  const double floor = TDB_PIVOT_FLOOR * wave_max_dpp(l < n ? fmax(x, 0.0) : 0.0);
+  const bool ok = wave_panel<S, RD>(A, Li, n, 0, floor);
+  if (Gi && ok) wave_inv_gram<1>(Li, Gi, n);
+  wave_fence();
+  return ok;
+}
+template <bool RD>
+__device__ __forceinline__ bool wave_chol_inv_2(double* A, int n, double* Li, double* Gi) {
+  const int l = threadIdx.x & 63;
+  const double x = A[min(l, n - 1) * (n + 1)];
+  const double floor = TDB_PIVOT_FLOOR * wave_max_dpp(l < n ? fmax(x, 0.0) : 0.0);
+  bool ok = wave_panel<16, RD>(A, Li, n, 0, floor);
+  auto at = [&](const double* M, int i, int j) {      // zero outside the matrix
+    const double m = M[min(i, n - 1) * n + min(j, n - 1)];
+    return (i < n && j < n) ? m : 0.0;
+  };
+  // A_11 -= L_10 L_10^T and X_10 = -L_10 X_00
+  wd4 c;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) c[i] = at(A, 16 + (l >> 4) + 4 * i, 16 + (l & 15));
+  c = mm16<16>([&](int i, int k) { return -at(A, 16 + i, k); }, [&](int k, int j) { return at(A, 16 + j, k); }, c);
+  const wd4 y = mm16<16>([&](int i, int k) { return -at(A, 16 + i, k); }, [&](int k, int j) { return at(Li, k, j); },
+                         (wd4){0, 0, 0, 0});
+  wave_fence();
+  each16(c, [&](int i, int j, double v) {
+    if (16 + i < n && 16 + j < n) A[(16 + i) * n + 16 + j] = v;
+  });
+  each16(y, [&](int i, int j, double v) {
+    if (16 + i < n) Li[(16 + i) * n + j] = v;
+  });
+  wave_fence();
+  ok = (n <= 20 ? wave_panel<4, RD>(A, Li, n, 16, floor)
+                : n <= 24 ? wave_panel<8, RD>(A, Li, n, 16, floor) : wave_panel<16, RD>(A, Li, n, 16, floor)) && ok;
+  if (Gi && ok) wave_inv_gram<2>(Li, Gi, n);
+  wave_fence();
+  return ok;
+}
+
+// 32 < n <= 64 (out of line: rare and long; the matrices may lie in global memory).
+static __device__ __attribute__((noinline)) bool wave_chol_inv_big(double* A, int n, double* Li, double* Gi) {
+  const int l = threadIdx.x & 63, nb = (n + 15) >> 4;
+  const double dx = A[min(l, n - 1) * (n + 1)];
+  const double floor = TDB_PIVOT_FLOOR * wave_max_dpp(l < n ? fmax(dx, 0.0) : 0.0);
+  auto at = [&](const double* M, int i, int j) {
+    const double m = M[min(i, n - 1) * n + min(j, n - 1)];
+    return (i < n && j < n) ? m : 0.0;
+  };
+  bool ok = true;
+  for (int kb = 0; kb < nb; ++kb) {
+    // lane l: row l of the panel's columns
+    const int k0 = 16 * kb;
+    double v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const double x = A[min(l, n - 1) * n + min(k0 + j, n - 1)];
+      v[j] = (l < n && k0 + j < n) ? x : (l == k0 + j ? 1.0 : 0.0);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const double piv = lane_get(v[k], k0 + k);
+      ok = ok && (k0 + k >= n || (piv > floor && piv > 0.0));
+      const double lk = sqrt(fmax(piv, 1e-300));
+      v[k] = l == k0 + k ? lk : v[k] / lk;
+#pragma unroll
+      for (int j = k + 1; j < 16; ++j) v[j] = fma(-v[k], lane_get(v[k], k0 + j), v[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+      if (l < n && k0 + j < n) A[l * n + k0 + j] = k0 + j <= l ? v[j] : 0.0;
+    wave_fence();
+    for (int ib = kb + 1; ib < nb; ++ib)
+      for (int jb = kb + 1; jb <= ib; ++jb) {
+        const int i0 = 16 * ib, j0 = 16 * jb;
+        wd4 c;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = at(A, i0 + (l >> 4) + 4 * i, j0 + (l & 15));
+        c = mm16<16>([&](int i, int k) { return -at(A, i0 + i, k0 + k); },
+                     [&](int k, int j) { return at(A, j0 + j, k0 + k); }, c);
+        each16(c, [&](int i, int j, double x) {
+          if (i0 + i < n && j0 + j < n) A[(i0 + i) * n + j0 + j] = x;
+        });
+      }
+    wave_fence();
+  }
+  if (!ok) return false;
+  for (int ib = 0; ib < nb; ++ib) {
+    // rows i0 .. i0 + 15 of the inverse: the sums over the earlier rows, then lane l column l
+    const int i0 = 16 * ib;
+    for (int jb = 0; jb < ib; ++jb) {
+      wd4 r = {0, 0, 0, 0};
+      for (int kb = jb; kb < ib; ++kb)
+        r = mm16<16>([&](int i, int k) { return at(A, i0 + i, 16 * kb + k); },
+                     [&](int k, int j) { return at(Li, 16 * kb + k, 16 * jb + j); }, r);
+      each16(r, [&](int i, int j, double x) {
+        if (i0 + i < n) Li[(i0 + i) * n + 16 * jb + j] = x;
+      });
+    }
+    wave_fence();
+    double s[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const double x = Li[min(i0 + i, n - 1) * n + min(l, n - 1)];
+      s[i] = l < i0 ? x : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const double lii = i0 + i < n ? A[min(i0 + i, n - 1) * (n + 1)] : 1.0;
+      const double num = l == i0 + i ? 1.0 : -s[i];
+      const double y = l <= i0 + i ? num / lii : 0.0;
+      s[i] = y;
+#pragma unroll
+      for (int m = i + 1; m < 16; ++m) s[m] = fma(A[min(i0 + m, n - 1) * n + min(i0 + i, n - 1)], y, s[m]);
+    }
+    wave_fence();
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (l < n && i0 + i < n) Li[(i0 + i) * n + l] = s[i];
+    wave_fence();
+  }
+  if (Gi) {
+    if (n <= 48) wave_inv_gram<3>(Li, Gi, n);
+    else wave_inv_gram<4>(Li, Gi, n);
+  }
+  wave_fence();
+  return true;
+}
+
+// Lower Cholesky factor of the SPD n x n matrix A (n <= 64, LDS, row stride n) in place, zeros
+// above, its inverse Li (RD: see wave_panel) and, with Gi, Gi = Li^T Li, by one full wave (no
+// lane may be masked off). Returns false if a pivot is not positive or not above
+// TDB_PIVOT_FLOOR times the largest diagonal entry; Gi is then not formed.
+template <bool RD>
 __device__ __forceinline__ bool wave_chol_inv(double* A, int n, double* Li, double* Gi) {
-  if (n <= 16) return wave_chol_inv_nb<1>(A, n, n, Li, Gi);
-  if (n <= 32) return wave_chol_inv_nb<2>(A, n, n, Li, Gi);
+  if (n <= 4) return wave_chol_inv_s<4, RD>(A, n, Li, Gi);
+  if (n <= 8) return wave_chol_inv_s<8, RD>(A, n, Li, Gi);
+  if (n <= 16) return wave_chol_inv_s<16, RD>(A, n, Li, Gi);
+  if (n <= 32) return wave_chol_inv_2<RD>(A, n, Li, Gi);
   return wave_chol_inv_big(A, n, Li, Gi);
 }
 

@@ -46,26 +46,6 @@ __device__ __forceinline__ EigWs eig_ws(const EigArgs& a) {
   return w;
 }
 
-// The reduction's sums keep the tree of halved lane distances. (The trailing eigenvectors of
-// a Gram matrix whose small eigenvalues lie close together are determined only to the
-// rounding of the tridiagonal matrix over their gaps: another order of these sums, as in a
-// form with a row per wave and no barriers, 3.8 us a launch, turns them by up to 1e-3, which
-// streams at fixed ranks on such directions carry into their reconstructions.)
-__device__ __forceinline__ double tree_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  return v;
-}
-__device__ __forceinline__ double tree_block_sum(double v, double* scratch) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  v = tree_sum(v);
-  if (lane == 0) scratch[wid] = v;
-  __syncthreads();
-  double s = 0.0;
-  for (int i = 0; i < nw; ++i) s += scratch[i];   // same order in every thread
-  __syncthreads();
-  return s;
-}
-
 // Step k of the distributed reduction for one mode, as workgroup bx of nblk.
 // Every global load of a step (the previous reflector and its product, row k, and this
 // workgroup's rows of the trailing block) is issued at entry into registers: one round
@@ -114,7 +94,7 @@ __device__ __forceinline__ void tri_step_body(const EigArgs& a, int k, int bx, i
         pvv += pl[u] * vl[u];
       }
     }
-    pvv = tree_block_sum(pvv, red);
+    pvv = block_sum(pvv, red);
     const double Kc = 0.5 * bp * pvv;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -137,7 +117,7 @@ __device__ __forceinline__ void tri_step_body(const EigArgs& a, int k, int bx, i
       ss += x * x;
     }
   }
-  ss = tree_block_sum(ss, red);
+  ss = block_sum(ss, red);
   const double x0 = v[0];
   double dk = dk0;
   if (bp != 0.0) dk -= vp[0] * wp[0] + wp[0] * vp[0];
@@ -179,7 +159,7 @@ __device__ __forceinline__ void tri_step_body(const EigArgs& a, int k, int bx, i
           if (j < m) sv += rv[q][c] * v[j];
         }
       }
-      sv = tree_sum(sv);
+      sv = warp_sum(sv);
       if (lane == 0) pk[k + 1 + i] = bk * sv;
     }
   }
@@ -253,7 +233,7 @@ __global__ void __launch_bounds__(TT_THREADS) k_tri_tail(EigBatch batch) {
       v[i] = vi;
       pvv += pp[k0 + i] * vi;
     }
-    pvv = tree_block_sum(pvv, red);
+    pvv = block_sum(pvv, red);
     const double Kc = 0.5 * bp * pvv;
     for (int i = tid; i < T; i += blockDim.x) wv[i] = pp[k0 + i] - Kc * v[i];
     __syncthreads();
@@ -273,7 +253,7 @@ __global__ void __launch_bounds__(TT_THREADS) k_tri_tail(EigBatch batch) {
       v[i] = x;
       ss += x * x;
     }
-    ss = tree_block_sum(ss, red);
+    ss = block_sum(ss, red);
     const double x0 = v[0];
     double bk = 0.0, ek = x0;
     if (ss > 0.0) {
@@ -313,7 +293,7 @@ __global__ void __launch_bounds__(TT_THREADS) k_tri_tail(EigBatch batch) {
         wv[tid] = pi;
         pv = pi * v[tid];
       }
-      pv = tree_block_sum(pv, red);
+      pv = block_sum(pv, red);
       const double Kc = 0.5 * bk * pv;
       if (tid < m) wv[tid] -= Kc * v[tid];
       __syncthreads();

@@ -618,7 +618,7 @@ __device__ __forceinline__ void ffinish_body(const FFinishArgs& a, int stage, Ct
   auto pinv = [&](const double* Csrc) {
     gram_from(Csrc, rn, R, inner, G, Gp);
     if (threadIdx.x < 64) {
-      const bool ok = wave_chol_inv(G, rn, Li, Gi);
+      const bool ok = wave_chol_inv<false>(G, rn, Li, Gi);
       if (threadIdx.x == 0) {
         ok_s = ok ? 1 : 0;
         if (!ok) atomicOr(&ctrl->numeric, 1);
@@ -762,11 +762,53 @@ struct QrRows {
 };
 
 // Partial Gram sum_q w_q u_q u_q^T of nr rows of rn entries in LDS on the matrix cores;
-// emit(r, c, v) for r >= c. part: FQR_GP doubles of LDS.
+// emit(r, c, v) for r >= c. An entry is the sum of w u_c times u_r over every fourth row from
+// row 0, 1, 2 and 3, the rows left over behind the first of these, added as
+// (s0 + s1) + (s2 + s3): a fixed order for the streams that turn its roundings into changes
+// that can be seen. A single block of 16 takes a wave for each of the four sums, otherwise a
+// wave takes a block. part: FQR_GP doubles of LDS.
 template <typename Emit>
 __device__ __forceinline__ void qr_gram(int rn, int nr, const double* Ul, const double* Wl, double* part, Emit emit) {
-  block_xyt_f64(rn, nr, true, [&](int i, int q) { return Wl[q * rn + i]; },
-                [&](int j, int q) { return Ul[q * rn + j]; }, emit, part);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int lm = lane & 15, lk = lane >> 4;
+  const int nb = (rn + 15) >> 4, n4 = nr >> 2;
+  auto sum = [&](int m, int r, int c) {
+    const double *u = Ul + r, *w = Wl + c;
+    md4 acc = wave_tile(0, n4, [&](int k) { return u[(4 * k + m) * rn]; }, [&](int k) { return w[(4 * k + m) * rn]; },
+                        (md4){0.0, 0.0, 0.0, 0.0});
+    if (m == 0)
+      acc = wave_tile(0, nr - 4 * n4, [&](int k) { return u[(4 * n4 + k) * rn]; },
+                      [&](int k) { return w[(4 * n4 + k) * rn]; }, acc);
+    return acc;
+  };
+  if (nb == 1) {
+    if (wid < 4) {
+      const int i = min(lm, rn - 1);
+      const md4 acc = sum(wid, i, i);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) part[wid * 256 + (lk + 4 * v) * 16 + lm] = acc[v];
+    }
+    __syncthreads();
+    const int t = threadIdx.x, r = t >> 4, c = t & 15;
+    if (r < rn && c <= r) emit(r, c, (part[t] + part[256 + t]) + (part[512 + t] + part[768 + t]));
+    __syncthreads();
+    return;
+  }
+  for (int blk = wid; blk < nb * (nb + 1) / 2; blk += nw) {
+    int bi = 0;
+    while ((bi + 1) * (bi + 2) / 2 <= blk) ++bi;
+    const int bj = blk - bi * (bi + 1) / 2;
+    const int i = min(16 * bi + lm, rn - 1), j = min(16 * bj + lm, rn - 1);
+    md4 s[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) s[m] = sum(m, i, j);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * bi + lk + 4 * v, c = 16 * bj + lm;
+      if (r < rn && c < rn && r >= c) emit(r, c, (s[0][v] + s[1][v]) + (s[2][v] + s[3][v]));
+    }
+  }
+  __syncthreads();
 }
 
 __device__ __forceinline__ void fqr_body(const FQrArgs& a, CtrlState* ctrl, int bx) {
@@ -916,15 +958,10 @@ __device__ __forceinline__ void fqr_body(const FQrArgs& a, CtrlState* ctrl, int 
     const int rm = wid == 0 ? r0 : (wid == 1 ? r1 : r2);
     double* Lm = wid == 0 ? L0 : (wid == 1 ? L1 : L2);
     double* Lig = wid == 0 ? a.Li[0] : (wid == 1 ? a.Li[1] : a.Li[2]);
-    bool ok;
-    if (a.li_off >= 0) {
-      double* Ll = lds + a.li_off + wid * rq * rq;
-      ok = wave_chol_inv(Lm, rm, Ll, nullptr);
-      if (ok)
-        for (int t = threadIdx.x & 63; t < rm * rm; t += 64) Lig[t] = Ll[t];
-    } else {
-      ok = wave_chol_inv_big(Lm, rm, Lig, nullptr);
-    }
+    double* Ll = a.li_off >= 0 ? lds + a.li_off + wid * rq * rq : Lig;
+    const bool ok = wave_chol_inv<true>(Lm, rm, Ll, nullptr);
+    if (ok && Ll != Lig)
+      for (int t = threadIdx.x & 63; t < rm * rm; t += 64) Lig[t] = Ll[t];
     if ((threadIdx.x & 63) == 0) ok_s[wid] = ok ? 1 : 0;
   }
   __syncthreads();
@@ -1238,7 +1275,7 @@ __device__ __forceinline__ void fpost_body(const FPostArgs& a, CtrlState* ctrl, 
           ctrl->sigma[n][i] = i < rn ? sqrt(fmax(lam[i], 0.0)) : 0.0;
       }
       bool ok = true;
-      if (need_p) ok = wave_chol_inv(G, rn, Li, Gi);
+      if (need_p) ok = wave_chol_inv<false>(G, rn, Li, Gi);
       if (threadIdx.x == 0) {
         ok_s = ok ? 1 : 0;
         if (!ok) atomicOr(&ctrl->numeric, 4);

@@ -82,16 +82,14 @@ struct CtrlState {
 // a NaN stays NaN (fmax(NaN, 0) would turn non-finite data into a zero error).
 __device__ __forceinline__ double sqrt_sum_sq(double x) { return x >= 0.0 ? sqrt(x) : (x < 0.0 ? 0.0 : x); }
 
-// Sum over the 64 lanes of a full wave, in every lane and in a fixed order: four steps
-// within the rows of 16 lanes on the data-parallel primitives (lane pairs, quads, halves,
-// rows), then the four rows. (Through LDS permutes a sum takes six dependent LDS round
-// trips.)
+// Value of v in another lane by a data-parallel primitive (CTRL), and in lane `l` (uniform) as a
+// wave-uniform value.
 template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
+__device__ __forceinline__ double dpp_get(double v) {
   const long long b = __double_as_longlong(v);
   const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
-  return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 __device__ __forceinline__ double lane_get(double v, int l) {
   const long long b = __double_as_longlong(v);
@@ -99,12 +97,29 @@ __device__ __forceinline__ double lane_get(double v, int l) {
   const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
+// Sum over the 64 lanes of a full wave, in every lane: lanes a distance of 32, 16, 8, 4, 2 and
+// 1 apart added in turn, on the lane primitives (through LDS permutes a sum takes six
+// dependent LDS round trips). The order is part of the results: errors decide against
+// thresholds, and the eigensolver's sums turn the trailing eigenvectors of close eigenvalues
+// (by up to 1e-3 in an order of another tree).
 __device__ __forceinline__ double warp_sum(double v) {
-  v = dpp_add<0xB1>(v);    // quad_perm 1 0 3 2
-  v = dpp_add<0x4E>(v);    // quad_perm 2 3 0 1
-  v = dpp_add<0x141>(v);   // row_half_mirror
-  v = dpp_add<0x140>(v);   // row_mirror
-  return (lane_get(v, 0) + lane_get(v, 16)) + (lane_get(v, 32) + lane_get(v, 48));
+  {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    v = __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+  }
+  {
+    const long long b = __double_as_longlong(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    v = __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+  }
+  v += dpp_get<0x128>(v);                 // row_ror 8
+  v += dpp_get<0x1B>(dpp_get<0x141>(v));  // row_half_mirror, then quad_perm 3 2 1 0: lane ^ 4
+  v += dpp_get<0x4E>(v);                  // quad_perm 2 3 0 1
+  v += dpp_get<0xB1>(v);                  // quad_perm 1 0 3 2
+  return v;
 }
 
 // Block-wide sum (blockDim.x a multiple of 64, <= 1024); result valid in all threads. The

@@ -22,6 +22,7 @@ struct TtmJob {
 // Products that do not depend on each other, in one launch.
 struct TtmGroup {
   int n;
+  int chain;   // every output one chain over the contracted rows in order
   TtmJob j[TTM_JOBS];
 };
 

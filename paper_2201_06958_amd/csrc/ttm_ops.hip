@@ -432,7 +432,8 @@ static hipError_t launch_as(const TtmGroup& g, hipStream_t s) {
   // A launch that leaves compute units without a block splits its contractions: four times
   // the blocks, a quarter of the serial rows each (400 x 200 x 12 at ranks (12, 11, 3), 118
   // blocks: a step 209 -> 173 us). With a block for every unit it does not: each block
-  // stages the matrix again (channel, 439 blocks of 48 outputs: 26 -> 50 us).
+  // stages the matrix again (channel, 439 blocks of 48 outputs: 26 -> 50 us). Nor where the
+  // caller asks for one chain an output (the core of the HOSVD: see wave_chol_inv).
   for (int ks = 0; ks < 2; ++ks) {
     L.n = 0;
     for (int q = 0; q < g.n; ++q) {
@@ -441,10 +442,10 @@ static hipError_t launch_as(const TtmGroup& g, hipStream_t s) {
       const int n = L.n++;
       L.j[n] = g.j[q];
       L.cut[n] = cut_of(g.j[q], OT, vec_of<TX>(), sizeof(TX), sizeof(TY), g.j[q].Y, ks != 0,
-                        ks_fits<T, OT, vec_of<TX>()>());
+                        !g.chain && ks_fits<T, OT, vec_of<TX>()>());
       L.start[n + 1] = L.start[n] + L.cut[n].blocks * L.cut[n].oblocks;
     }
-    if (L.start[L.n] >= 256) break;
+    if (g.chain || L.start[L.n] >= 256) break;
   }
   if (!L.n) return hipSuccess;
   for (; L.first < L.start[L.n]; L.first += TTM_GRID)

@@ -1,0 +1,105 @@
+"""Core and bases of third-order streams, bit for bit. Where a stream holds directions near
+the noise floor, one rounding of the FP64 work between its passes grows into changes of the
+reconstruction that can be seen, so the order of those operations is part of the result:
+the digests are those of the state with the operations one after another as device_util.h
+states them. The snapshots are sums and products of small integers, exact in FP32 and the
+same everywhere, with noise in their last bits that the chosen ranks reach into."""
+import hashlib
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2201_06958_amd import load_library
+    load_library()
+
+
+def snapshots(dims, seed, count=4, terms=3):
+    rng = np.random.default_rng(seed)
+    f = [rng.integers(-8, 9, size=(terms, n)) for n in dims]
+    out = []
+    for k in range(count):
+        amp = np.array([2 ** (11 - 4 * m) for m in range(terms)]) + k * rng.integers(-3, 4, size=terms)
+        v = np.zeros(dims, dtype=np.int64)
+        for m in range(terms):
+            v += amp[m] * f[0][m][:, None, None] * f[1][m][None, :, None] * f[2][m][None, None, :]
+        out.append(v + rng.integers(-3, 4, size=dims))
+    return out
+
+
+def digest(handle):
+    _, C, U = handle.get_core_and_bases()
+    h = hashlib.sha256(np.ascontiguousarray(C).tobytes())
+    for u in U:
+        h.update(np.ascontiguousarray(u).tobytes())
+    return h.hexdigest()[:16]
+
+
+def config(dims, ranks, data, prec, **kw):
+    return dict(dims=dims, dt=2.0 ** -9, rank_max=ranks, rank_init=ranks, data_dtype=data, precision=prec,
+                adaptive=False, eps_th=1.0, **kw)
+
+
+def device(v, data):
+    return torch.from_numpy(v.astype(np.float32 if data == "f32" else np.float64)).to("cuda")
+
+
+# dims, ranks (one block of the factorisations with few and with 16 steps, two, more), types
+SINGLE = [
+    ((65, 33, 6), (3, 4, 2), "f32", "f32", "f1e3e9e620be275f c9e2909bc9c3f4ce"),
+    ((70, 40, 8), (10, 10, 3), "f32", "bf16s", "069e1bd472afaa8b 519e513cae818419"),
+    ((64, 48, 8), (16, 15, 8), "f64", "f64", "79481832c8d06c2f 8b75716210949439"),
+    ((90, 75, 8), (18, 20, 4), "f32", "f32", "ddaa181c90e0f0cd 0273ff32e36360a2"),
+    ((90, 75, 12), (24, 32, 5), "f64", "f64", "1267f10c48b995d5 6eacf8d12ac6f0c4"),
+    ((80, 70, 4), (40, 36, 4), "f32", "f32", "795da3407b895fda 4ca05521e28e9712"),
+]
+
+
+def run_single(dims, ranks, data, prec):
+    from paper_2201_06958_amd import Compressor
+    v = [device(x, data) for x in snapshots(dims, sum(dims) + sum(ranks))]
+    c = Compressor(**config(dims, ranks, data, prec)).init(v[0])
+    d = [digest(c)]
+    for x in v[1:]:
+        c.ingest(x)
+    d.append(digest(c))
+    c.close()
+    return " ".join(d)
+
+
+@pytest.mark.parametrize("dims,ranks,data,prec,want", SINGLE)
+def test_single_stream(dims, ranks, data, prec, want):
+    print("case", dims, ranks, data, prec, flush=True)
+    assert run_single(dims, ranks, data, prec) == want
+
+
+BATCH = [
+    (((48, 33, 8), (64, 40, 8), (40, 70, 8)), (10, 10, 3), "f32", "bf16s",
+     "4020ec53b6573916 aa277309d28f8533 390eb3126831d78a"),
+    (((48, 33, 6), (64, 40, 6)), (20, 18, 6), "f64", "f64", "24d5bc5084f54d9f 084cb36fe81d3f37"),
+]
+
+
+def run_batch(dims, ranks, data, prec):
+    from paper_2201_06958_amd import Batch
+    v = [[device(x, data) for x in snapshots(d, sum(d) + i)] for i, d in enumerate(dims)]
+    b = Batch([config(d, ranks, data, prec) for d in dims]).init([x[0] for x in v])
+    for k in range(1, len(v[0])):
+        b.ingest([x[k] for x in v])
+    d = " ".join(digest(s) for s in b.streams)
+    b.close()
+    return d
+
+
+@pytest.mark.parametrize("dims,ranks,data,prec,want", BATCH)
+def test_batch(dims, ranks, data, prec, want, monkeypatch):
+    monkeypatch.setenv("TDB_AUTOTUNE", "0")   # one plan: another orders the sums of the passes differently
+    print("case", dims, ranks, data, prec, flush=True)
+    assert run_batch(dims, ranks, data, prec) == want
