@@ -302,8 +302,8 @@ tdb_status tdb_batch_flush(tdb_batch b);
  * (pass_kind 2; pass_cols columns of mode 2 per workgroup), matrix-core tiles (1) or
  * vector-ALU tiles (0); the error pass takes column blocks of the mode-1 unfolding
  * (err_kind 1) or row slabs (0). With more than one candidate, each is timed on the
- * first snapshots (the pass over three launches after one untimed; the partials only,
- * no state changes) and the fastest kept; the choice is cached for the process per
+ * first snapshots (the shortest of four averages over three launches after one untimed;
+ * the partials only, no state changes) and the fastest kept; the choice is cached for the process per
  * shape class (storage and compute types, the members' extents and caps).
  * source: 0 the fixed rule (TDB_AUTOTUNE=0 in the environment, or TDB_RPASS_COLS
  * forcing the column count), 1 timed at creation,
