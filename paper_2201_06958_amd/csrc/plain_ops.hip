@@ -497,13 +497,18 @@ __global__ void __launch_bounds__(256) k_qr_gram(PlainArgs a, CtrlState* ctrl) {
 // Block n: the factor L of U_n^T W_n U_n = L L^T (R_n = L^T) and its inverse; the identity
 // when the step is not applied. After one round the bases are orthonormal to cond(U)^2
 // roundings, so a second one matters only where the Gram is far from the identity;
-// qneed then asks for it.
+// qneed then asks for it. The flags are read once a block, so that its waves take one branch,
+// and without NUM_BASIS, which the other blocks of this launch may be raising.
 __global__ void __launch_bounds__(256) k_qr_fact(PlainArgs a, CtrlState* ctrl) {
   __shared__ double A[TDB_RCAP * PLD], Li[TDB_RCAP * PLD];
   __shared__ double red[16];
   const int n = blockIdx.x, rn = a.r[n];
   const int slabs = (int)((a.N[n] + PL_QSLAB - 1) / PL_QSLAB);
-  const bool skip = (ctrl->numeric & ~NUM_NEXT) != 0;
+  __shared__ int flags;
+  if (threadIdx.x == 0)
+    flags = __hip_atomic_load(&ctrl->numeric, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ~(NUM_NEXT | NUM_BASIS);
+  __syncthreads();
+  const bool skip = flags != 0;
   bool ok = false;
   double dev = 0.0;
   if (!skip) {
