@@ -78,11 +78,11 @@ template hipError_t launch_fd2<double>(const double*, const double*, const doubl
                                        double, hipStream_t);
 
 // Bound by the host link at large states, by the launch at small ones.
-__global__ void __launch_bounds__(256) k_pack(PackArgs a, double* __restrict__ out, long long tot) {
-  for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < tot; t += (long long)gridDim.x * 256) {
-    long long q = t - a.csz;
+__global__ void __launch_bounds__(256) k_pack(PackArgs a, double* __restrict__ out, long long t0, long long cnt) {
+  for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < cnt; t += (long long)gridDim.x * 256) {
+    long long q = t0 + t - a.csz;
     if (q < 0) {
-      out[t] = a.C[t];
+      out[t] = a.C[t0 + t];
       continue;
     }
     int n = 0;
@@ -95,11 +95,11 @@ __global__ void __launch_bounds__(256) k_pack(PackArgs a, double* __restrict__ o
   }
 }
 
-hipError_t launch_pack(const PackArgs& a, double* out, long long tot, hipStream_t s) {
-  if (tot <= 0) return hipSuccess;
-  long long blocks = (tot + 255) / 256;
+hipError_t launch_pack(const PackArgs& a, double* out, long long t0, long long cnt, hipStream_t s) {
+  if (cnt <= 0) return hipSuccess;
+  long long blocks = (cnt + 255) / 256;
   if (blocks > 2048) blocks = 2048;
-  hipLaunchKernelGGL(k_pack, dim3((unsigned)blocks), dim3(256), 0, s, a, out, tot);
+  hipLaunchKernelGGL(k_pack, dim3((unsigned)blocks), dim3(256), 0, s, a, out, t0, cnt);
   return hipGetLastError();
 }
 

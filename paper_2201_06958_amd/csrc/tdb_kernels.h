@@ -36,9 +36,10 @@ hipError_t launch_nonfinite_check(const T* x, long long n, int* flag, hipStream_
 // D1 = (V1 - Vm) / (2 dt) at t_k, D2 = (3 V1 - 4 V0 + Vm) / (2 dt) at t_{k+1}.
 template <typename T>
 hipError_t launch_fd2(const T* Vm, const T* V0, const T* V1, T* D1, T* D2, long long n, double dt, hipStream_t s);
-// The core (csz entries) and the bases (N[n] x r[n], stored with leading dimension ldU[n])
-// dense and one after another into out (tot doubles; device or pinned host memory).
-constexpr long long PACK_PINNED = 1 << 21;   // doubles of pinned memory a handle may hold for it
+// The core (csz entries) and the bases (N[n] x r[n], stored with leading dimension ldU[n]),
+// dense and one after another: entries t0 .. t0 + cnt of that sequence to out (device or pinned
+// host memory).
+constexpr long long PACK_PINNED = 1 << 17;   // doubles of pinned memory of a handle for it (1 MB)
 struct PackArgs {
   int p;
   long long csz, N[TDB_P];
@@ -46,7 +47,7 @@ struct PackArgs {
   const double* C;
   const double* U[TDB_P];
 };
-hipError_t launch_pack(const PackArgs& a, double* out, long long tot, hipStream_t s);
+hipError_t launch_pack(const PackArgs& a, double* out, long long t0, long long cnt, hipStream_t s);
 
 // ---- HOSVD (hosvd_ops.hip)
 struct HosvdModeArgs {

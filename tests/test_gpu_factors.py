@@ -1,4 +1,8 @@
-"""Core and bases read to the host: the energetic rotation in every order and precision."""
+"""Core and bases read to the host: states below and above the pinned buffer they go through,
+what a caller leaves out, and the energetic rotation in every order and precision."""
+import ctypes
+import threading
+
 import numpy as np
 import pytest
 
@@ -59,4 +63,65 @@ def test_rotation(dims, ranks, prec):
     # the state is untouched
     _, C1, U1 = c.get_core_and_bases()
     assert np.array_equal(C0, C1) and all(np.array_equal(a, b) for a, b in zip(U0, U1))
+    c.close()
+
+
+HALF = 1 << 16     # doubles of a half of the pinned buffer
+
+
+@pytest.mark.parametrize("dims,ranks", [
+    (((HALF - 64) // 8 - 9, 8), (8, 8)),       # one piece, short of a half
+    (((HALF - 64 - 64) // 8, 8), (8, 8)),      # exactly a half
+    (((HALF - 64 - 64) // 8 + 1, 8), (8, 8)),  # the last basis ends in a second piece
+    ((HALF // 8 * 3 + 5, 8), (8, 8)),          # four pieces
+    ((100, 90, 80), (50, 40, 41)),             # the core alone more than a half
+    ((40, 39, 38, 37), (20, 20, 17, 16)),
+])
+def test_read_in_pieces(dims, ranks):
+    print("case", dims, ranks, flush=True)
+    rng = np.random.default_rng(4)
+    core = rng.normal(size=ranks)
+    c, U = stream(dims, ranks, "f32", core)
+    for _ in range(2):
+        r, C1, U1 = c.get_core_and_bases()
+        assert r == ranks and np.array_equal(C1, core) and all(np.array_equal(a, b) for a, b in zip(U1, U))
+    # any of the outputs may be left out
+    P = ctypes.POINTER(ctypes.c_double)
+    for skip in range(-1, len(dims)):
+        got = [np.full(u.shape, np.nan) for u in U]
+        Cg = np.full(ranks, np.nan)
+        uptr = (P * 8)()
+        for n, u in enumerate(got):
+            if n != skip:
+                uptr[n] = u.ctypes.data_as(P)
+        assert c.lib.tdb_get_core_and_bases(c.h, 0, None, None if skip < 0 else Cg.ctypes.data_as(P), uptr) == 0
+        assert np.isnan(Cg).all() if skip < 0 else np.array_equal(Cg, core)
+        for n, (a, b) in enumerate(zip(got, U)):
+            assert np.isnan(a).all() if n == skip else np.array_equal(a, b)
+    assert c.lib.tdb_get_core_and_bases(c.h, 0, None, None, None) == 0
+    c.close()
+
+
+def test_read_takes_no_device_memory():
+    """A state of 128 MB is read without a device allocation: the free memory that another
+    thread sees during the call stays what it was (within 32 MB for the runtime's own)."""
+    rng = np.random.default_rng(5)
+    c, U = stream((2_000_000, 8), (8, 8), "f32", np.diag(2.0 ** -np.arange(8)))
+    c.get_core_and_bases()
+    torch.cuda.synchronize()
+    least, done = [torch.cuda.mem_get_info()[0]], threading.Event()
+    before = least[0]
+
+    def watch():
+        while not done.is_set():
+            least[0] = min(least[0], torch.cuda.mem_get_info()[0])
+
+    t = threading.Thread(target=watch)
+    t.start()
+    for _ in range(3):
+        _, C1, U1 = c.get_core_and_bases()
+    done.set()
+    t.join()
+    assert all(np.array_equal(a, b) for a, b in zip(U1, U))
+    assert before - least[0] < 32 << 20, (before, least[0])
     c.close()
