@@ -888,9 +888,9 @@ __device__ __forceinline__ void fqr_body(const FQrArgs& a, CtrlState* ctrl, int 
         if (i != j) g[j * rn + i] = v;
       });
     }
-    // the last block factors the three Grams and folds the core: the barrier and thread
-    // 0's release make the partials visible with the count, its acquire and the second
-    // barrier let the whole block read the others'
+    // the last block factors the three Grams and folds the core: every wave releases its own
+    // partials before the block counts, and acquires the others' once it is known to be last
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (threadIdx.x == 0) {
       const unsigned prev = __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
@@ -898,6 +898,7 @@ __device__ __forceinline__ void fqr_body(const FQrArgs& a, CtrlState* ctrl, int 
     }
     __syncthreads();
     if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (threadIdx.x == 0) *a.counter = 0u;
     if (skip) return;
     {

@@ -103,3 +103,11 @@ def test_batch(dims, ranks, data, prec, want, monkeypatch):
     monkeypatch.setenv("TDB_AUTOTUNE", "0")   # one plan: another orders the sums of the passes differently
     print("case", dims, ranks, data, prec, flush=True)
     assert run_batch(dims, ranks, data, prec) == want
+
+
+def test_same_bits_from_many_slabs():
+    """A single stream's QR adds partial Grams of 64 rows that as many workgroups write and the
+    last of them reads: the same snapshots give the same state every time."""
+    print("case many slabs", flush=True)
+    seen = {run_single((512, 450, 8), (18, 17, 4), "f32", "f32") for _ in range(8)}
+    assert len(seen) == 1
