@@ -12,6 +12,7 @@
 #include "tdb_common.h"
 #include "device_util.h"
 #include "ttm.h"
+#include <type_traits>
 
 namespace tdb {
 
@@ -144,14 +145,19 @@ __device__ __forceinline__ void ttm_cols(const TtmJob& j, long long unit0, int o
     if (k0) __syncthreads();
     stage_m<T, OT>(j, k0, kc, o0, Ml);
     __syncthreads();
-    for (int k = kw; k < kc; k += STEP) {
+    // one turn; tail: rows past the last are its copies, and zeros take their place (a zero of
+    // the matrix times an infinity would be NaN)
+    auto turn = [&](int k, auto tail) {
       T d[RG][4][V];
 #pragma unroll
       for (int g = 0; g < RG; ++g)
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
-          for (int v = 0; v < V; ++v) d[g][s][v] = X0 ? (T)x[g][s][v] - (T)y[g][s][v] : (T)x[g][s][v];
+          for (int v = 0; v < V; ++v) {
+            d[g][s][v] = X0 ? (T)x[g][s][v] - (T)y[g][s][v] : (T)x[g][s][v];
+            if (tail.value) d[g][s][v] = k0 + k + 16 * g + 4 * s + kg < j.Nin ? d[g][s][v] : (T)0;
+          }
       load(k0 + (k + STEP < kc ? k + STEP : kc + kw));
 #pragma unroll
       for (int g = 0; g < RG; ++g) {
@@ -168,6 +174,10 @@ __device__ __forceinline__ void ttm_cols(const TtmJob& j, long long unit0, int o
 #pragma unroll
             for (int v = 0; v < V; ++v) acc[t][v] = Acc<T>::mma(m[t][s], d[g][s][v], acc[t][v]);
       }
+    };
+    for (int k = kw; k < kc; k += STEP) {
+      if (k0 + k + 16 * RG <= j.Nin) turn(k, std::false_type{});
+      else turn(k, std::true_type{});
     }
   }
   if constexpr (KS) {

@@ -66,6 +66,31 @@ def test_rotation(dims, ranks, prec):
     c.close()
 
 
+@pytest.mark.parametrize("dims,ranks", [
+    ((70, 40), (5, 3)),                    # one contracted tile, not full
+    ((300, 270), (33, 18)),                # several, and rows past the last
+    ((40, 36, 12), (6, 5, 4)),
+    ((40, 130, 20), (20, 90, 9)),
+    ((9, 20, 18, 5), (3, 7, 5, 2)),
+])
+@pytest.mark.parametrize("out", ["f32", "f64"])
+def test_infinite_entries_stay_infinite(dims, ranks, out):
+    """One infinite entry of the core, the last, and factors without zeros: every value of the
+    reconstruction is an infinity of the sign that its product has."""
+    from paper_2201_06958_amd.tdb import reconstruct_noalloc
+    print("case", dims, ranks, out, flush=True)
+    rng = np.random.default_rng(sum(dims))
+    C = rng.uniform(0.5, 1.0, size=ranks)
+    C[(-1,) * len(ranks)] = np.inf
+    U = [rng.uniform(0.5, 1.0, size=(n, r)) * rng.choice([-1.0, 1.0], size=(n, r)) for n, r in zip(dims, ranks)]
+    sign = np.sign(U[0][:, -1])
+    for u in U[1:]:
+        sign = sign[..., None] * np.sign(u[:, -1])
+    V = torch.empty(dims, dtype=torch.float32 if out == "f32" else torch.float64, device="cuda")
+    reconstruct_noalloc(torch.from_numpy(C).cuda(), [torch.from_numpy(u).cuda() for u in U], V)
+    assert np.array_equal(V.cpu().numpy(), sign * np.inf)
+
+
 HALF = 1 << 16     # doubles of a half of the pinned buffer
 
 
