@@ -35,8 +35,9 @@ struct TtmErr {
   double* partials;
 };
 
-// TX: input type, T: arithmetic type, TY: output type.
-template <typename TX, typename T, typename TY>
+// TX: input type, T: type of the products, TY: output type, S: type of the sums over more than a
+// few rows.
+template <typename TX, typename T, typename TY, typename S = T>
 hipError_t launch_ttm_group(const TtmGroup& g, hipStream_t s);
 // The product of `j` against the snapshot; *blocks receives the number of partial
 // pairs, at most ttm_err_blocks() of the same job.

@@ -5,8 +5,8 @@
 //
 // A product over the middle index of (A, Nin, Bsz) is, for each a, a matrix product of
 // M^T (Nout x Nin) with the Nin x Bsz slice, so the 16x16x4 matrix instructions take M as
-// the A operand and 16 columns of the slice as the B operand. FP32 products accumulate
-// in FP32 and FP64 products in FP64, as the arithmetic type asks. One thread per output
+// the A operand and 16 columns of the slice as the B operand. Products and sums are of the
+// arithmetic type; FP32 products may be summed in FP64. One thread per output
 // (the earlier form) read every operand from the caches once per output: 81 us a product
 // on average for the 192 x 129 x 192 x 3 FP32 channel at ranks (33, 13, 33, 3).
 #include "tdb_common.h"
@@ -35,6 +35,23 @@ template <> struct Acc<double> {
   }
   static __device__ __forceinline__ int row(int kg, int i) { return kg + 4 * i; }
 };
+
+// A run of 16 contracted rows: products and their sums within it in T, the sum over the runs
+// in S. (With S = T the runs are one chain. FP32 products with FP64 sums: a third-order step of
+// 192^3 FP32 at ranks 5 takes 189 us, 206 on the FP64 matrix cores, 184 with FP32 sums of
+// whole modes, which were up to ten times as far off.)
+template <typename T, typename S>
+__device__ __forceinline__ void begin_run(const typename Acc<S>::v& acc, typename Acc<T>::v& run) {
+  if constexpr (std::is_same<T, S>::value) run = acc;
+  else run = (typename Acc<T>::v){0, 0, 0, 0};
+}
+template <typename T, typename S>
+__device__ __forceinline__ void end_run(const typename Acc<T>::v& run, typename Acc<S>::v& acc) {
+  if constexpr (std::is_same<T, S>::value) acc = run;
+  else
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] += (S)run[i];
+}
 
 // Columns a lane takes from one 16-byte load of X.
 template <typename TX> constexpr int vec_of() { return 16 / (int)sizeof(TX); }
@@ -72,8 +89,8 @@ template <typename T, int OT, int V> constexpr bool ks_fits() { return 1024 * OT
 // Adds the four waves' accumulators of 16 V columns (in wave order, through 1024 OT V values
 // of LDS) and hands each lane the sums of its V columns: fn(output, values), thread t's
 // outputs being t / 16 + 16 q.
-template <typename T, int OT, int V, typename Fn>
-__device__ __forceinline__ void ks_sum(T* lds, const typename Acc<T>::v (&acc)[OT][V], Fn fn) {
+template <typename T, typename S, int OT, int V, typename Fn>
+__device__ __forceinline__ void ks_sum(S* lds, const typename Acc<S>::v (&acc)[OT][V], Fn fn) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = lane & 15, kg = lane >> 4;
   constexpr int W = 256 * OT * V;
 #pragma unroll
@@ -86,10 +103,10 @@ __device__ __forceinline__ void ks_sum(T* lds, const typename Acc<T>::v (&acc)[O
 #pragma unroll
   for (int q = 0; q < OT; ++q) {
     const int e = (int)threadIdx.x + 256 * q;
-    T val[V];
+    S val[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      const T* l = lds + v * 256 * OT + e;
+      const S* l = lds + v * 256 * OT + e;
       val[v] = ((l[0] + l[W]) + l[2 * W]) + l[3 * W];
     }
     fn(e >> 4, val);
@@ -104,7 +121,7 @@ __device__ __forceinline__ void ks_sum(T* lds, const typename Acc<T>::v (&acc)[O
 // read once), latency for the later ones.
 // KS: the four waves of a block share one unit and split its contracted rows (every
 // fourth 16 of them), and their sums are added through LDS in wave order.
-template <typename TX, typename T, int V, int RG, int OT, bool KS, typename Emit>
+template <typename TX, typename T, typename S, int V, int RG, int OT, bool KS, typename Emit>
 __device__ __forceinline__ void ttm_cols(const TtmJob& j, long long unit0, int o0, T* Ml, Emit emit) {
   typedef TX vx __attribute__((ext_vector_type(V)));
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -121,11 +138,11 @@ __device__ __forceinline__ void ttm_cols(const TtmJob& j, long long unit0, int o
   const long long base = a * j.Nin * j.Bsz + bc;
   const TX* X = static_cast<const TX*>(j.X) + base;
   const TX* X0 = j.X0 ? static_cast<const TX*>(j.X0) + base : nullptr;
-  typename Acc<T>::v acc[OT][V];
+  typename Acc<S>::v acc[OT][V];
 #pragma unroll
   for (int t = 0; t < OT; ++t)
 #pragma unroll
-    for (int v = 0; v < V; ++v) acc[t][v] = (typename Acc<T>::v){0, 0, 0, 0};
+    for (int v = 0; v < V; ++v) acc[t][v] = (typename Acc<S>::v){0, 0, 0, 0};
   vx x[RG][4], y[RG][4];
   auto load = [&](int k) {
 #pragma unroll
@@ -167,12 +184,21 @@ __device__ __forceinline__ void ttm_cols(const TtmJob& j, long long unit0, int o
         for (int t = 0; t < OT; ++t)
 #pragma unroll
           for (int s = 0; s < 4; ++s) m[t][s] = Ml[(((k >> 4) + g) * (OT * 16) + 16 * t + c) * 16 + kg * 4 + s];
+        typename Acc<T>::v run[OT][V];
+#pragma unroll
+        for (int t = 0; t < OT; ++t)
+#pragma unroll
+          for (int v = 0; v < V; ++v) begin_run<T, S>(acc[t][v], run[t][v]);
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
           for (int t = 0; t < OT; ++t)
 #pragma unroll
-            for (int v = 0; v < V; ++v) acc[t][v] = Acc<T>::mma(m[t][s], d[g][s][v], acc[t][v]);
+            for (int v = 0; v < V; ++v) run[t][v] = Acc<T>::mma(m[t][s], d[g][s][v], run[t][v]);
+#pragma unroll
+        for (int t = 0; t < OT; ++t)
+#pragma unroll
+          for (int v = 0; v < V; ++v) end_run<T, S>(run[t][v], acc[t][v]);
       }
     };
     for (int k = kw; k < kc; k += STEP) {
@@ -182,7 +208,7 @@ __device__ __forceinline__ void ttm_cols(const TtmJob& j, long long unit0, int o
   }
   if constexpr (KS) {
     __syncthreads();
-    ks_sum<T, OT, V>(Ml, acc, [&](int o, const T(&val)[V]) {
+    ks_sum<T, S, OT, V>(reinterpret_cast<S*>(Ml), acc, [&](int o, const S(&val)[V]) {
       if (b < j.Bsz && o0 + o < j.Nout) emit(a, o0 + o, b, (a * j.Nout + o0 + o) * j.Bsz + b, val);
     });
     return;
@@ -194,7 +220,7 @@ __device__ __forceinline__ void ttm_cols(const TtmJob& j, long long unit0, int o
     for (int i = 0; i < 4; ++i) {
       const int o = o0 + 16 * t + Acc<T>::row(kg, i);
       if (o < j.Nout) {
-        T val[V];
+        S val[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) val[v] = acc[t][v][i];
         emit(a, o, b, (a * j.Nout + o) * j.Bsz + b, val);
@@ -207,7 +233,7 @@ __device__ __forceinline__ void ttm_cols(const TtmJob& j, long long unit0, int o
 // tile per wave. The slices are padded so that the 16 columns a wave reads at a time fall
 // into different banks for Bsz = 1. KS: 16 columns a block, its waves splitting the rows
 // of each chunk.
-template <typename TX, typename T, int OT, bool KS, typename Emit>
+template <typename TX, typename T, typename S, int OT, bool KS, typename Emit>
 __device__ __forceinline__ void ttm_rows(const TtmJob& j, long long a0, int o0, T* Ml, T* Xl, Emit emit) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int c = lane & 15, kg = lane >> 4;
@@ -221,9 +247,9 @@ __device__ __forceinline__ void ttm_rows(const TtmJob& j, long long a0, int o0, 
   const int al = cc / B, bl = cc - al * B;
   const TX* X = static_cast<const TX*>(j.X);
   const TX* X0 = static_cast<const TX*>(j.X0);
-  typename Acc<T>::v acc[OT][1];
+  typename Acc<S>::v acc[OT][1];
 #pragma unroll
-  for (int t = 0; t < OT; ++t) acc[t][0] = (typename Acc<T>::v){0, 0, 0, 0};
+  for (int t = 0; t < OT; ++t) acc[t][0] = (typename Acc<S>::v){0, 0, 0, 0};
   T buf[NL];
   const int row = j.Nin * B;                       // values of a slice
   auto load = [&](int k0) {
@@ -256,19 +282,24 @@ __device__ __forceinline__ void ttm_rows(const TtmJob& j, long long a0, int o0, 
     if (k0 + TTM_KS < j.Nin) load(k0 + TTM_KS);
     const T* xp = Xl + al * P + bl;
     for (int k = KS ? 16 * wv : 0; k < kc; k += KS ? 64 : 16) {
+      typename Acc<T>::v run[OT];
+#pragma unroll
+      for (int t = 0; t < OT; ++t) begin_run<T, S>(acc[t][0], run[t]);
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         const T d = xp[(k + 4 * s + kg) * B];
 #pragma unroll
         for (int t = 0; t < OT; ++t)
-          acc[t][0] = Acc<T>::mma(Ml[((k >> 4) * (OT * 16) + 16 * t + c) * 16 + kg * 4 + s], d, acc[t][0]);
+          run[t] = Acc<T>::mma(Ml[((k >> 4) * (OT * 16) + 16 * t + c) * 16 + kg * 4 + s], d, run[t]);
       }
+#pragma unroll
+      for (int t = 0; t < OT; ++t) end_run<T, S>(run[t], acc[t][0]);
     }
   }
   const long long a = a0 + al;
   if constexpr (KS) {
     __syncthreads();
-    ks_sum<T, OT, 1>(Ml, acc, [&](int o, const T(&val)[1]) {
+    ks_sum<T, S, OT, 1>(reinterpret_cast<S*>(Ml), acc, [&](int o, const S(&val)[1]) {
       if (col < ta * B && o0 + o < j.Nout) emit(a, o0 + o, (long long)bl, (a * j.Nout + o0 + o) * B + bl, val);
     });
     return;
@@ -280,7 +311,7 @@ __device__ __forceinline__ void ttm_rows(const TtmJob& j, long long a0, int o0, 
     for (int i = 0; i < 4; ++i) {
       const int o = o0 + 16 * t + Acc<T>::row(kg, i);
       if (o < j.Nout) {
-        T val[1] = {acc[t][0][i]};
+        S val[1] = {acc[t][0][i]};
         emit(a, o, (long long)bl, (a * j.Nout + o) * j.Bsz + bl, val);
       }
     }
@@ -304,7 +335,7 @@ struct TtmLaunch {
 
 constexpr int TTM_XBYTES(int elem) { return (64 * TTM_KS + 64 * 4 + 16) * elem; }
 
-template <typename TX, typename T, typename TY, int OT>
+template <typename TX, typename T, typename TY, typename S, int OT>
 __global__ void __launch_bounds__(256) k_ttm_mm(TtmLaunch g) {
   __shared__ __align__(16) unsigned char raw[TTM_MBYTES + TTM_XBYTES(sizeof(T))];
   T* Ml = reinterpret_cast<T*>(raw);
@@ -321,26 +352,26 @@ __global__ void __launch_bounds__(256) k_ttm_mm(TtmLaunch g) {
   TY* Y = static_cast<TY*>(j.Y);
   if (cut.vec == V) {
     typedef TY vy __attribute__((ext_vector_type(V)));
-    auto put = [&](long long, int, long long, long long at, const T(&val)[V]) {
+    auto put = [&](long long, int, long long, long long at, const S(&val)[V]) {
       vy v;
 #pragma unroll
       for (int k = 0; k < V; ++k) v[k] = (TY)val[k];
       *reinterpret_cast<vy*>(Y + at) = v;
     };
-    if constexpr (ks_fits<T, OT, V>())
+    if constexpr (ks_fits<S, OT, V>())
       if (cut.ks) {
-        ttm_cols<TX, T, V, 1, OT, true>(j, cb, o0, Ml, put);
+        ttm_cols<TX, T, S, V, 1, OT, true>(j, cb, o0, Ml, put);
         return;
       }
-    ttm_cols<TX, T, V, 1, OT, false>(j, cb * 4, o0, Ml, put);
+    ttm_cols<TX, T, S, V, 1, OT, false>(j, cb * 4, o0, Ml, put);
   } else {
-    auto put = [&](long long, int, long long, long long at, const T(&val)[1]) { Y[at] = (TY)val[0]; };
+    auto put = [&](long long, int, long long, long long at, const S(&val)[1]) { Y[at] = (TY)val[0]; };
     if (cut.vec == 1) {
-      if (cut.ks) ttm_cols<TX, T, 1, 1, OT, true>(j, cb, o0, Ml, put);
-      else ttm_cols<TX, T, 1, 2, OT, false>(j, cb * 4, o0, Ml, put);
+      if (cut.ks) ttm_cols<TX, T, S, 1, 1, OT, true>(j, cb, o0, Ml, put);
+      else ttm_cols<TX, T, S, 1, 2, OT, false>(j, cb * 4, o0, Ml, put);
     } else {
-      if (cut.ks) ttm_rows<TX, T, OT, true>(j, cb * (16 / j.Bsz), o0, Ml, Xl, put);
-      else ttm_rows<TX, T, OT, false>(j, cb * (64 / j.Bsz), o0, Ml, Xl, put);
+      if (cut.ks) ttm_rows<TX, T, S, OT, true>(j, cb * (16 / j.Bsz), o0, Ml, Xl, put);
+      else ttm_rows<TX, T, S, OT, false>(j, cb * (64 / j.Bsz), o0, Ml, Xl, put);
     }
   }
 }
@@ -368,18 +399,18 @@ __global__ void __launch_bounds__(256) k_ttm_err(TtmLaunch g, TtmErr e) {
   };
   if (cut.vec == V) {
     typedef TV vv __attribute__((ext_vector_type(V)));
-    ttm_cols<TX, T, V, 1, OT, false>(j, cb * 4, o0, Ml, [&](long long a, int o, long long b, long long at, const T(&val)[V]) {
+    ttm_cols<TX, T, T, V, 1, OT, false>(j, cb * 4, o0, Ml, [&](long long a, int o, long long b, long long at, const T(&val)[V]) {
       const double wr = e.wa[a] * e.wo[o];
       const vv x = *reinterpret_cast<const vv*>(S + at);
 #pragma unroll
       for (int k = 0; k < V; ++k) add(wr, b + k, x[k], val[k]);
     });
   } else if (cut.vec == 1) {
-    ttm_cols<TX, T, 1, 2, OT, false>(j, cb * 4, o0, Ml, [&](long long a, int o, long long b, long long at, const T(&val)[1]) {
+    ttm_cols<TX, T, T, 1, 2, OT, false>(j, cb * 4, o0, Ml, [&](long long a, int o, long long b, long long at, const T(&val)[1]) {
       add(e.wa[a] * e.wo[o], b, S[at], val[0]);
     });
   } else {
-    ttm_rows<TX, T, OT, false>(j, cb * (64 / j.Bsz), o0, Ml, Xl,
+    ttm_rows<TX, T, T, OT, false>(j, cb * (64 / j.Bsz), o0, Ml, Xl,
                         [&](long long a, int o, long long b, long long at, const T(&val)[1]) {
                           add(e.wa[a] * e.wo[o], b, S[at], val[0]);
                         });
@@ -436,7 +467,7 @@ static bool job_ok(const TtmJob& j) {
   return j.A >= 1 && j.Bsz >= 1 && j.Nin >= 1 && j.Nout >= 1 && j.X && j.M;
 }
 
-template <typename TX, typename T, typename TY, int OT>
+template <typename TX, typename T, typename TY, typename S, int OT>
 static hipError_t launch_as(const TtmGroup& g, hipStream_t s) {
   TtmLaunch L{};
   // A launch that leaves compute units without a block splits its contractions: four times
@@ -452,29 +483,32 @@ static hipError_t launch_as(const TtmGroup& g, hipStream_t s) {
       const int n = L.n++;
       L.j[n] = g.j[q];
       L.cut[n] = cut_of(g.j[q], OT, vec_of<TX>(), sizeof(TX), sizeof(TY), g.j[q].Y, ks != 0,
-                        !g.chain && ks_fits<T, OT, vec_of<TX>()>());
+                        !g.chain && ks_fits<S, OT, vec_of<TX>()>());
       L.start[n + 1] = L.start[n] + L.cut[n].blocks * L.cut[n].oblocks;
     }
     if (g.chain || L.start[L.n] >= 256) break;
   }
   if (!L.n) return hipSuccess;
   for (; L.first < L.start[L.n]; L.first += TTM_GRID)
-    hipLaunchKernelGGL((k_ttm_mm<TX, T, TY, OT>), dim3(grid_of(L.start[L.n] - L.first)), dim3(256), 0, s, L);
+    hipLaunchKernelGGL((k_ttm_mm<TX, T, TY, S, OT>), dim3(grid_of(L.start[L.n] - L.first)), dim3(256), 0, s, L);
   return hipGetLastError();
 }
 
-template <typename TX, typename T, typename TY>
+template <typename TX, typename T, typename TY, typename S>
 hipError_t launch_ttm_group(const TtmGroup& g, hipStream_t s) {
   if (g.n < 0 || g.n > TTM_JOBS) return hipErrorInvalidValue;
-  hipError_t e = launch_as<TX, T, TY, 4>(g, s);
-  if (e == hipSuccess) e = launch_as<TX, T, TY, 3>(g, s);
-  if (e == hipSuccess) e = launch_as<TX, T, TY, 2>(g, s);
-  if (e == hipSuccess) e = launch_as<TX, T, TY, 1>(g, s);
+  hipError_t e = launch_as<TX, T, TY, S, 4>(g, s);
+  if (e == hipSuccess) e = launch_as<TX, T, TY, S, 3>(g, s);
+  if (e == hipSuccess) e = launch_as<TX, T, TY, S, 2>(g, s);
+  if (e == hipSuccess) e = launch_as<TX, T, TY, S, 1>(g, s);
   return e;
 }
 template hipError_t launch_ttm_group<float, float, float>(const TtmGroup&, hipStream_t);
 template hipError_t launch_ttm_group<double, float, float>(const TtmGroup&, hipStream_t);
 template hipError_t launch_ttm_group<float, float, double>(const TtmGroup&, hipStream_t);
+template hipError_t launch_ttm_group<float, double, float>(const TtmGroup&, hipStream_t);
+template hipError_t launch_ttm_group<float, float, float, double>(const TtmGroup&, hipStream_t);
+template hipError_t launch_ttm_group<double, float, float, double>(const TtmGroup&, hipStream_t);
 template hipError_t launch_ttm_group<float, double, double>(const TtmGroup&, hipStream_t);
 template hipError_t launch_ttm_group<double, double, double>(const TtmGroup&, hipStream_t);
 template hipError_t launch_ttm_group<double, double, float>(const TtmGroup&, hipStream_t);
