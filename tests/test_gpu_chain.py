@@ -107,6 +107,31 @@ def test_single_stream_matches_oracle(dims, ranks, mode):
     c.close()
 
 
+@pytest.mark.parametrize("dims,ranks,path", [((30, 200, 40), (24, 20, 6), "auto"), ((20, 18, 64), (6, 5, 17), "auto"),
+                                             ((70, 40, 20), (33, 32, 9), "auto"), ((9, 20, 18, 5), (4, 7, 6, 3), "auto")])
+def test_buffers_made_on_a_side_stream(dims, ranks, path):
+    """The products' buffers are made by the first step that takes them, which may run on a
+    stream of its own: the same as on the null stream, bit for bit."""
+    from paper_2201_06958_amd import Compressor
+    print("case", dims, ranks, flush=True)
+    v = [torch.from_numpy(np.ascontiguousarray(x)).to("cuda") for x in walk(dims, ranks, 5)]
+    got = []
+    for side in (False, True):
+        c = Compressor(dims, 1e-2, rank_max=ranks, rank_init=ranks, data_dtype="f64", precision="f64", path=path,
+                       adaptive=False)
+        c.init(v[0])
+        torch.cuda.synchronize()
+        s = torch.cuda.Stream() if side else torch.cuda.default_stream()
+        with torch.cuda.stream(s):
+            for x in v[1:]:
+                c.ingest(x, stream=s)
+        torch.cuda.synchronize()
+        _, C, U = c.get_core_and_bases()
+        got.append((C, U))
+        c.close()
+    assert np.array_equal(got[0][0], got[1][0]) and all(np.array_equal(a, b) for a, b in zip(got[0][1], got[1][1]))
+
+
 @pytest.mark.parametrize("prec", ["f64", "f32"])
 @pytest.mark.parametrize("shapes,ranks", [
     (((20, 18, 192), (33, 24, 192)), (5, 5, 5)),      # tiles shrunk along modes 1 and 2 to fit the LDS
