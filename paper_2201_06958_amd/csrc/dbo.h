@@ -3,10 +3,9 @@
 // grouped into one mode of N1 N2 rows. V is M x K row-major (the tall mode first, the
 // short mode of K <= 32 entries unit-stride); the ranks are equal, r1 = r2 = r <= K.
 //
-// A step walks the rows of V a few times, each row handled by one thread (the short
-// mode and the ranks live in registers), with the sums over rows formed per block in
-// LDS in a fixed order; single-block FP64 kernels do the r x r work between the row
-// passes. The reinitialisation takes the tall mode's basis from the short mode's
+// A step walks the rows of V a few times, 16 rows a wave with every product of a row on the
+// matrix cores, and the sums over rows formed per block in a fixed order; single-block FP64
+// kernels do the r x r work between the row passes. The reinitialisation takes the tall mode's basis from the short mode's
 // eigenvectors, U1 = V W2 U2 Sigma^-1 (the left singular vectors of the weighted
 // unfolding), so no Gram of the tall mode is ever formed.
 #pragma once
@@ -50,7 +49,7 @@ struct DboArgs {
   int ldU1, ldU2;        // leading dimensions of U1, U2 (the caps)
   int full2;             // r == K: the short mode's basis derivative vanishes
   int euler;             // explicit Euler (one stage)
-  int TR;                // rows per chunk (rows staged in LDS together)
+  int TR;                // rows of a block at a time (dbo_rows; the HOSVD map stages them in LDS)
   int nblk;              // row blocks launched (partial-sum slots)
   int caps;              // HOSVD: columns of the basis at the caps
   double dt, dscale;     // step; 1/dt for a difference of snapshots, 1 for a derivative

@@ -98,7 +98,6 @@ hipError_t noalloc_reconstruct(const NoallocPlan& pl, const long long* dims, con
     TtmJob& j = g.j[0];
     j.X = in;
     j.M = U[k];
-    j.m64 = 1;
     j.ms_i = 1;
     j.ms_o = ranks[k];
     j.A = A;

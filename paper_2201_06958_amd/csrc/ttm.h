@@ -8,15 +8,15 @@ constexpr int TTM_JOBS = 4;
 
 // One product Y[a, o, b] = sum_i M(i, o) X[a, i, b] on a C-ordered tensor viewed as
 // (A, Nin, Bsz); with X0 the input is X - X0. M(i, o) = M[i * ms_i + o * ms_o], times
-// mw[i] when mw is given; M is FP64 or the arithmetic type (m64).
+// mw[i] when mw is given.
 struct TtmJob {
   const void* X;
   const void* X0;
-  const void* M;
+  const double* M;
   const double* mw;
   void* Y;
   long long A, Bsz, ms_i, ms_o;
-  int Nin, Nout, m64;
+  int Nin, Nout;
 };
 
 // Products that do not depend on each other, in one launch.

@@ -76,7 +76,7 @@ __device__ __forceinline__ void stage_m(const TtmJob& j, int k0, int kc, int o0,
     double v = 0.0;
     if (gk < j.Nin && go < j.Nout) {
       const long long e = (long long)gk * j.ms_i + (long long)go * j.ms_o;
-      v = j.m64 ? static_cast<const double*>(j.M)[e] : (double)static_cast<const T*>(j.M)[e];
+      v = j.M[e];
       if (j.mw) v *= j.mw[gk];
     }
     Ml[((k >> 4) * (OT * 16) + o) * 16 + (k & 3) * 4 + ((k & 15) >> 2)] = (T)v;
