@@ -494,9 +494,50 @@ static hipError_t launch_as(const TtmGroup& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+// One output a thread, its sum in order, eight rows' loads at a time: for expansions of a small
+// core, where staging M and a wave's tiles cost more than they save. The same sums as
+// k_ttm_mm's, bit for bit.
+template <typename TX, typename T, typename TY>
+__global__ void __launch_bounds__(256) k_ttm_each(TtmJob j, unsigned total) {
+  const unsigned t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= total) return;
+  const unsigned B = (unsigned)j.Bsz, ao = t / B, b = t - ao * B, a = ao / (unsigned)j.Nout, o = ao - a * (unsigned)j.Nout;
+  const TX* x = static_cast<const TX*>(j.X) + (size_t)a * j.Nin * B + b;
+  const double* m = j.M + (long long)o * j.ms_o;
+  T acc = (T)0;
+  int i = 0;
+  for (; i + 8 <= j.Nin; i += 8) {
+    TX xv[8];
+    double mv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      xv[u] = x[(size_t)(i + u) * B];
+      mv[u] = m[(i + u) * j.ms_i];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc = fma((T)mv[u], (T)xv[u], acc);
+  }
+  for (; i < j.Nin; ++i) acc = fma((T)m[i * j.ms_i], (T)x[(size_t)i * B], acc);
+  static_cast<TY*>(j.Y)[t] = (TY)acc;
+}
+// Up to 10 M multiply-adds: the whole decode of 512 x 500 at ranks 24 takes 13.2 us (16.7 in
+// tiles), 50 x 48 x 50 x 4 at (20, 18, 16, 4), 10 M in its last product, 22.9 (28.4); above it
+// 160^3 at 24, 15 M in its second product, 55.3 (51.4), 120 x 100 x 90 at 22, 24 M, 38.2 (26.8).
+constexpr long long TTM_EACH = 10000000;
+static bool each_ok(const TtmGroup& g) {
+  if (g.n != 1) return false;
+  const TtmJob& j = g.j[0];
+  return !j.X0 && !j.mw && job_ok(j) && j.Y && j.Nin <= 64 && j.A * j.Nout * j.Bsz <= TTM_EACH / j.Nin;
+}
+
 template <typename TX, typename T, typename TY, typename S>
 hipError_t launch_ttm_group(const TtmGroup& g, hipStream_t s) {
   if (g.n < 0 || g.n > TTM_JOBS) return hipErrorInvalidValue;
+  if (each_ok(g)) {
+    const unsigned total = (unsigned)(g.j[0].A * g.j[0].Nout * g.j[0].Bsz);
+    hipLaunchKernelGGL((k_ttm_each<TX, T, TY>), dim3((total + 255) / 256), dim3(256), 0, s, g.j[0], total);
+    return hipGetLastError();
+  }
   hipError_t e = launch_as<TX, T, TY, S, 4>(g, s);
   if (e == hipSuccess) e = launch_as<TX, T, TY, S, 3>(g, s);
   if (e == hipSuccess) e = launch_as<TX, T, TY, S, 2>(g, s);

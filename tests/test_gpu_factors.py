@@ -91,6 +91,31 @@ def test_infinite_entries_stay_infinite(dims, ranks, out):
     assert np.array_equal(V.cpu().numpy(), sign * np.inf)
 
 
+@pytest.mark.parametrize("dims,ranks", [
+    ((3, 2), (1, 1)), ((64, 512), (8, 20)), ((100, 9, 7, 5), (9, 9, 7, 1)), ((100, 60, 80), (10, 24, 20)),   # one output a thread
+    ((500, 500), (40, 40)), ((501, 499), (41, 39)),                 # the last product at the limit, and above
+    ((3001, 170), (21, 20)), ((45, 37, 33, 15), (9, 17, 16, 15)),   # tiles with remainders
+    ((64, 60, 62, 8), (20, 24, 18, 6)), ((90, 101, 103), (22, 23, 24)),
+])
+@pytest.mark.parametrize("out", ["f32", "f64"])
+def test_decode_matches_64_bits(dims, ranks, out):
+    """Each product of r terms adds at most (r + 2) roundings of the sum of magnitudes; the
+    output one more in its own type. The output may lie off a 16-byte boundary."""
+    from paper_2201_06958_amd.tdb import reconstruct_noalloc
+    print("case", dims, ranks, out, flush=True)
+    rng = np.random.default_rng(sum(dims))
+    C, U = rng.normal(size=ranks), [rng.normal(size=(n, r)) for n, r in zip(dims, ranks)]
+    ref, mag = O.reconstruct(C, U), O.reconstruct(np.abs(C), [np.abs(u) for u in U])
+    bound = sum(r + 3 for r in ranks) * 2.0 ** -53 * 2 * mag + (2.0 ** -24 if out == "f32" else 0.0) * np.abs(ref)
+    S = int(np.prod(dims))
+    for off in (0, 1):
+        buf = torch.full((S + 4,), float("nan"), dtype=torch.float32 if out == "f32" else torch.float64, device="cuda")
+        V = buf[off:off + S].view(dims)
+        reconstruct_noalloc(torch.from_numpy(C).cuda(), [torch.from_numpy(u).cuda() for u in U], V)
+        assert (np.abs(V.cpu().numpy().astype(np.float64) - ref) <= bound).all()
+        assert torch.isnan(buf[:off]).all() and torch.isnan(buf[off + S:]).all()
+
+
 HALF = 1 << 16     # doubles of a half of the pinned buffer
 
 
