@@ -487,7 +487,7 @@ __device__ __forceinline__ bool wave_chol_inv_nb(double* A, int n, int ld, doubl
 // A 16x16x4 FP64 product is an ascending chain of fused multiply-adds, so it takes the place
 // of any run of such updates.
 // Bound by the dependent steps. With Gi: 1.0 us at n = 4, 1.6 at 8, 3.4 at 16, 5.9 at 18, 9.9 at
-// 32, 36 at 33 and 62 at 64; one lane per row with the inverse as a second substitution took
+// 32, 26 at 33 and 54 at 64; one lane per row with the inverse as a second substitution took
 // 5.7, 5.8, 6.0, 16.3 and 16.8, and with loops over LDS above 32 rows 95 and 388.
 
 // Largest of the lanes' values (none of them NaN), in every lane.
@@ -543,8 +543,8 @@ __device__ __forceinline__ bool wave_panel(double* A, double* Li, int n, int k0,
 }
 
 // Gi = Li^T Li (n <= 16 NB, row stride n), sums over the rows in order.
-template <int NB>
-__device__ __forceinline__ void wave_inv_gram(const double* Li, double* Gi, int n) {
+template <int NB, typename PL>
+__device__ __forceinline__ void wave_inv_gram(PL Li, PL Gi, int n) {
   auto at = [&](int i, int j) {
     const double x = Li[min(i, n - 1) * n + min(j, n - 1)];
     return (i < n && j < n) ? x : 0.0;
@@ -574,7 +574,7 @@ __device__ __forceinline__ bool wave_chol_inv_s(double* A, int n, double* Li, do
   const double x = A[min(l, n - 1) * (n + 1)];
   const double floor = TDB_PIVOT_FLOOR * wave_max_dpp(l < n ? fmax(x, 0.0) : 0.0);
   const bool ok = wave_panel<S, RD>(A, Li, n, 0, floor);
-  if (Gi && ok) wave_inv_gram<1>(Li, Gi, n);
+  if (Gi && ok) wave_inv_gram<1, double*>(Li, Gi, n);
   wave_fence();
   return ok;
 }
@@ -605,17 +605,20 @@ __device__ __forceinline__ bool wave_chol_inv_2(double* A, int n, double* Li, do
   wave_fence();
   ok = (n <= 20 ? wave_panel<4, RD>(A, Li, n, 16, floor)
                 : n <= 24 ? wave_panel<8, RD>(A, Li, n, 16, floor) : wave_panel<16, RD>(A, Li, n, 16, floor)) && ok;
-  if (Gi && ok) wave_inv_gram<2>(Li, Gi, n);
+  if (Gi && ok) wave_inv_gram<2, double*>(Li, Gi, n);
   wave_fence();
   return ok;
 }
 
-// 32 < n <= 64 (out of line: rare and long; the matrices may lie in global memory).
-static __device__ __attribute__((noinline)) bool wave_chol_inv_big(double* A, int n, double* Li, double* Gi) {
+// 32 < n <= 64 (out of line: rare and long). A in LDS, Li and Gi there too or anywhere (PL: the
+// pointers' type; through plain pointers every access would be a flat one).
+typedef __attribute__((address_space(3))) double lds_double;
+template <bool GRAM, typename PL>
+static __device__ __attribute__((noinline)) bool wave_chol_inv_big(lds_double* A, int n, PL Li, PL Gi) {
   const int l = threadIdx.x & 63, nb = (n + 15) >> 4;
   const double dx = A[min(l, n - 1) * (n + 1)];
   const double floor = TDB_PIVOT_FLOOR * wave_max_dpp(l < n ? fmax(dx, 0.0) : 0.0);
-  auto at = [&](const double* M, int i, int j) {
+  auto at = [&](auto M, int i, int j) {
     const double m = M[min(i, n - 1) * n + min(j, n - 1)];
     return (i < n && j < n) ? m : 0.0;
   };
@@ -631,8 +634,9 @@ static __device__ __attribute__((noinline)) bool wave_chol_inv_big(double* A, in
     }
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
+      if (k0 + k >= n) break;
       const double piv = lane_get(v[k], k0 + k);
-      ok = ok && (k0 + k >= n || (piv > floor && piv > 0.0));
+      ok = ok && piv > floor && piv > 0.0;
       const double lk = sqrt(fmax(piv, 1e-300));
       v[k] = l == k0 + k ? lk : v[k] / lk;
 #pragma unroll
@@ -670,20 +674,23 @@ static __device__ __attribute__((noinline)) bool wave_chol_inv_big(double* A, in
       });
     }
     wave_fence();
-    double s[16];
+    // (the rows of the diagonal block, one a lane, so that a coefficient is a lane's value)
+    double s[16], c[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const double x = Li[min(i0 + i, n - 1) * n + min(l, n - 1)];
       s[i] = l < i0 ? x : 0.0;
+      c[i] = A[min(i0 + (l & 15), n - 1) * n + min(i0 + i, n - 1)];
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const double lii = i0 + i < n ? A[min(i0 + i, n - 1) * (n + 1)] : 1.0;
+      if (i0 + i >= n) break;
+      const double lii = lane_get(c[i], i);
       const double num = l == i0 + i ? 1.0 : -s[i];
       const double y = l <= i0 + i ? num / lii : 0.0;
       s[i] = y;
 #pragma unroll
-      for (int m = i + 1; m < 16; ++m) s[m] = fma(A[min(i0 + m, n - 1) * n + min(i0 + i, n - 1)], y, s[m]);
+      for (int m = i + 1; m < 16; ++m) s[m] = fma(lane_get(c[i], m), y, s[m]);
     }
     wave_fence();
 #pragma unroll
@@ -691,25 +698,28 @@ static __device__ __attribute__((noinline)) bool wave_chol_inv_big(double* A, in
       if (l < n && i0 + i < n) Li[(i0 + i) * n + l] = s[i];
     wave_fence();
   }
-  if (Gi) {
-    if (n <= 48) wave_inv_gram<3>(Li, Gi, n);
-    else wave_inv_gram<4>(Li, Gi, n);
+  if (GRAM) {
+    if (n <= 48) wave_inv_gram<3, PL>(Li, Gi, n);
+    else wave_inv_gram<4, PL>(Li, Gi, n);
   }
   wave_fence();
   return true;
 }
 
 // Lower Cholesky factor of the SPD n x n matrix A (n <= 64, LDS, row stride n) in place, zeros
-// above, its inverse Li (RD: see wave_panel) and, with Gi, Gi = Li^T Li, by one full wave (no
-// lane may be masked off). Returns false if a pivot is not positive or not above
+// above, its inverse Li (RD: see wave_panel) and, unless RD, Gi = Li^T Li, by one full wave (no
+// lane may be masked off); Li and Gi in LDS unless FAR. Returns false if a pivot is not positive or not above
 // TDB_PIVOT_FLOOR times the largest diagonal entry; Gi is then not formed.
-template <bool RD>
+template <bool RD, bool FAR = false>
 __device__ __forceinline__ bool wave_chol_inv(double* A, int n, double* Li, double* Gi) {
   if (n <= 4) return wave_chol_inv_s<4, RD>(A, n, Li, Gi);
   if (n <= 8) return wave_chol_inv_s<8, RD>(A, n, Li, Gi);
   if (n <= 16) return wave_chol_inv_s<16, RD>(A, n, Li, Gi);
   if (n <= 32) return wave_chol_inv_2<RD>(A, n, Li, Gi);
-  return wave_chol_inv_big(A, n, Li, Gi);
+  // (RD: the caller wants no Gi)
+  lds_double* a = (lds_double*)A;
+  if (FAR) return wave_chol_inv_big<!RD>(a, n, Li, RD ? Li : Gi);
+  return wave_chol_inv_big<!RD>(a, n, (lds_double*)Li, (lds_double*)(RD ? Li : Gi));
 }
 
 // Whether the symmetric n x n matrix A (n <= 64, LDS, row-major, lower triangle read) is

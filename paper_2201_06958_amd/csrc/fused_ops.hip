@@ -959,10 +959,15 @@ __device__ __forceinline__ void fqr_body(const FQrArgs& a, CtrlState* ctrl, int 
     const int rm = wid == 0 ? r0 : (wid == 1 ? r1 : r2);
     double* Lm = wid == 0 ? L0 : (wid == 1 ? L1 : L2);
     double* Lig = wid == 0 ? a.Li[0] : (wid == 1 ? a.Li[1] : a.Li[2]);
-    double* Ll = a.li_off >= 0 ? lds + a.li_off + wid * rq * rq : Lig;
-    const bool ok = wave_chol_inv<true>(Lm, rm, Ll, nullptr);
-    if (ok && Ll != Lig)
-      for (int t = threadIdx.x & 63; t < rm * rm; t += 64) Lig[t] = Ll[t];
+    bool ok;
+    if (a.li_off >= 0) {
+      double* Ll = lds + a.li_off + wid * rq * rq;
+      ok = wave_chol_inv<true>(Lm, rm, Ll, nullptr);
+      if (ok)
+        for (int t = threadIdx.x & 63; t < rm * rm; t += 64) Lig[t] = Ll[t];
+    } else {
+      ok = wave_chol_inv<true, true>(Lm, rm, Lig, nullptr);
+    }
     if ((threadIdx.x & 63) == 0) ok_s[wid] = ok ? 1 : 0;
   }
   __syncthreads();
