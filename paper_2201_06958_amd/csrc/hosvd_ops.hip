@@ -202,7 +202,7 @@ __device__ void repair(const SelectArgs& a, int* r) {
 __device__ void greedy(const SelectArgs& a, int* r, double nu2, double B, double* red, int* grow) {
   // the energy within the ranks, then of what each growth adds (the whole sum at every growth
   // made the selection 168 us for 512 x 256 x 8 at ranks 18 x 17 x 4 and 4.8 ms for
-  // 192 x 129 x 192 x 3 at 33 x 13 x 33 x 3, now 69 and 236)
+  // 192 x 129 x 192 x 3 at 33 x 13 x 33 x 3, now 73 and 235, the truncation's 6 and 21 apart)
   double e = sub_energy(a.Cmax, a.caps, r, a.p, red);
   while (true) {
     const double e2 = fmax(nu2 - e, 0.0);

@@ -439,7 +439,8 @@ static bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_
 // accessed V values at a time as well. ks: contractions of 64 rows and more take a block per
 // unit, its waves splitting the rows. wide: with a quarter of the waves that the rule asks
 // for, 16-byte loads of rows split over a block's waves replace single columns (as many
-// blocks, four times the bytes a load: a 192^3 FP32 step at ranks 5 takes 184 us, 191 with single columns).
+// blocks, four times the bytes a load: a 192^3 FP32 step at ranks 5 took 184 us, 191 with single
+// columns, both with FP32 sums).
 static TtmCut cut_of(const TtmJob& j, int OT, int V, size_t xb, size_t yb, const void* Y, bool ks, bool wide) {
   TtmCut c;
   c.oblocks = (j.Nout + OT * 16 - 1) / (OT * 16);
